@@ -4,8 +4,7 @@
 Workload (the headline line): the walled cavity on a 1300 x 1300 grid with
 512 ordinates (8 Gauss-Legendre polar x 64 azimuths), minmod second order,
 Heun, CFL 0.5 (5200 steps to T = 2.6); each FP32 psi buffer holds 3.5 GB,
-far more than the 256 MB Infinity Cache. One step = both Heun stages (in one
-pass over psi with FP32 storage, in two launches with BF16) with their
+far more than the 256 MB Infinity Cache. One step = both Heun stages with their
 scalar-flux epilogues and QoI reductions over the whole grid. Inputs
 are synthetic (the problem statement itself) and resident in HBM before
 timing starts.
@@ -13,8 +12,8 @@ timing starts.
 Prints one JSON line. `value` = cell-ordinate updates per second (one update
 = one (cell, ordinate) advanced one full time step), timed over exactly
 --steps steps with no per-launch instrumentation. `roofline` describes the
-dominant kernel (the one-pass Heun step, or Heun stage 2) against 8 TB/s, its
-average duration taken with HIP events on the launch stream in a second, separately timed pass;
+dominant kernel (Heun stage 2; the one-pass Heun step in the Venkatakrishnan
+leg) against 8 TB/s, its average duration taken with HIP events on the launch stream in a second, separately timed pass;
 `step_roofline` is the whole step's algorithmic bytes over ms_per_step.
 `cpu_baseline` times the FP64 oracle on a bounded sample of the same
 workload on the host cores. Further keys time the 700^2 x 256 lattice, the

@@ -326,8 +326,8 @@ sn_status sn_plan_use_graph(sn_plan *plan, int32_t steps_per_graph);
  * stage launch on the launch stream. sn_plan_kernel_ms returns the summed
  * milliseconds and launch counts per kernel kind: index 0 = Euler stage,
  * 1 = Heun stage 1, 2 = Heun stage 2, 3 = QoI finalize. Plans that take a
- * Heun step in one pass over psi (FP32, no reflecting side, no probes, large
- * grids with minmod; the library's choice) count it under 2, and nothing under 1.
+ * Heun step in one pass over psi (FP32, orders 1 and 3, no reflecting side, no
+ * probes; the library's choice) count it under 2, and nothing under 1.
  * Synchronises. */
 sn_status sn_plan_set_timing(sn_plan *plan, int32_t on);
 sn_status sn_plan_kernel_ms(sn_plan *plan, double ms[4], int64_t counts[4]);

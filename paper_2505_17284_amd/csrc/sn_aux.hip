@@ -280,9 +280,7 @@ __device__ __forceinline__ void heun_finalize_block(HFArgs a, int blk, double* r
 #pragma unroll
     for (int t = 0; t < kMaxTallies; ++t) qa[t] = 0.0;
     // The groups' sum, s and the next emission in FP64: the scalar flux
-    // feeds back into every ordinate (whole solves of the 140^2 x 64 lattice
-    // end 0.5 10^-6 from FP64 in the median of twelve draws, 0.8 with FP32
-    // sums here, 0.8 with two stages; same time).
+    // feeds back into every ordinate, and the time is the same.
     auto sum_groups = [&](int64_t off, int g0, int g1, double (&v1)[4], double (&vg)[4]) {
         for (int g = g0; g < g1; g += 8) {  // eight groups' loads in flight
             float4 x[8], y[8];
@@ -635,14 +633,12 @@ hipError_t launch_ghost_fill(int dtype, const GhostArgs& a, hipStream_t s) {
 
 hipError_t launch_heun(int order, int waves, const HeunArgs& a, hipStream_t s) {
     if (order == 1) return launch_heun_o1(waves, a, s);
-    if (order == 2) return launch_heun_o2(waves, a, s);
     if (order == 3) return launch_heun_o3(waves, a, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_heun_batch(int order, int waves, int max_sides, const HeunBatch& L, hipStream_t s) {
     if (order == 1) return launch_heun_batch_o1(waves, max_sides, L, s);
-    if (order == 2) return launch_heun_batch_o2(waves, max_sides, L, s);
     if (order == 3) return launch_heun_batch_o3(waves, max_sides, L, s);
     return hipErrorInvalidValue;
 }

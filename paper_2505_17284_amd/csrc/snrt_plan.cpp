@@ -446,7 +446,7 @@ sn_status face_tables(sn_plan* P) {
     return SN_OK;
 }
 
-// The one-pass Heun step takes FP32 storage, orders 1 and 2 and vacuum or
+// The one-pass Heun step takes FP32 storage, orders 1 and 3 and vacuum or
 // inflow sides (a reflective side's ghost of psi1 is another ordinate's), no
 // probes, and rectangles whose sides normal to x lie in different groups of
 // four columns. Other statements keep the
@@ -486,19 +486,18 @@ bool heun_sides(sn_plan* P) {
 
 // Waves per workgroup and rows per band. A workgroup of w waves takes 2 w
 // ordinates; 16 waves halve the scalar-flux sums that 8 write, but leave one
-// workgroup per compute unit, which waits at its own barriers: measured 1-4%
-// faster from 1.2 10^5 cells on (lattice, 64 to 512 ordinates) and where the
-// ordinates are many (140^2 x 1936 160 us to 151), level or up to 20% slower
-// below (140^2 x 256 38.6 against 37.7), and 5-10% slower at order 3 (560^2 x 256 371 us against
-// 351, 1300^2 x 256 1747 against 1569). The band is the multiple of 4 up to 64 rows (the rows
-// between two barriers) with the least
+// workgroup per compute unit, which waits at its own barriers: measured (order 1,
+// lattice, us a step with 8 waves and with 16) 2-4% faster from 1.2 10^5 cells on
+// (437^2 x 128 64.9 and 63.2, 700^2 x 256 300 and 294, 1300^2 x 256 1111 and 1073)
+// and where the ordinates are many (140^2 x 1936 136 and 133), level or slower
+// below (280^2 x 128 41.2 and 41.0, 140^2 x 256 32.7 and 34.1), and 3-8% slower
+// at order 3 (560^2 x 256 319 and 334, 1300^2 x 256 1616 and 1744). The band is the
+// multiple of 4 up to 64 rows (the rows between two barriers) with the least
 //     rounds of workgroups x (rows + 12),
 // 12 rows standing for a march's start (its first loads, three rows before
 // the band) and its end, and a last round of x of the resident workgroups
 // counting 0.4 + 0.6 x: short bands fill the chip on small grids, tall ones
-// repeat less. Fitted to the lattice at 104 to 1300 columns with 32 to 512
-// ordinates (46 classes, up to 35 shapes each): within 4% of the fastest shape
-// on average, 30% at worst (140 columns, 512 ordinates).
+// repeat less.
 void heun_shape(sn_plan* P) {
     int quad[4] = {0, 0, 0, 0};
     for (int k = 0; k < P->M; ++k) quad[(P->xi[k] > 0 ? 1 : 0) + (P->eta[k] > 0 ? 2 : 0)]++;
@@ -624,21 +623,21 @@ sn_status derive(sn_plan* P, int group_size, int group_size_avg, int rows, int w
         o.fx = P->w[k] * std::fabs(P->xi[k]);
         o.fy = P->w[k] * std::fabs(P->eta[k]);
     }
-    // The one-pass Heun step (sn_heun_impl.h) wherever it can: it is faster at
-    // every size measured (lattice, order 2, us a step with the finalize
-    // against two stages: 437 x 437 x 128 66 to 118;
-    // 700 x 700 x 256 287 to 514; 1300 x 1300 x 512 cavity 1690 to 3480; order
-    // 3: 104 x 104 x 32 28 to 41, 700 x 700 x 256 588 to 768). Not
-    // with BF16 storage (g would be rounded before s is added), with a reflecting side (a ghost cell is then psi1 of
-    // another ordinate) or probes (their moments are of psi1).
-    // Minmod below 1.2 10^7 cell-ordinates keeps the two stages, although one
-    // pass would be faster there too (280 x 280 x 128 45 us to 65): whole solves
-    // of this size amplify any rounding at the limiter's switching points (256
-    // steps of 280 x 280 lattices end 4 to 9 10^-6 of phi from FP64, with FP64
-    // arithmetic on an FP32 state as well), and parameter studies made of them
-    // keep their results bit for bit.
-    const bool keeps_bits = P->order == 2 && (int64_t)P->nx * P->ny * P->M < 12000000;
-    P->heun1 = P->stepper == SN_HEUN && P->dtype == SN_F32 && P->n_probes == 0 && !keeps_bits;
+    // The one-pass Heun step (sn_heun_impl.h) at orders 1 and 3 wherever it
+    // can: it is faster at every size measured (order 3, us a step with the
+    // finalize against two stages: 104 x 104 x 32 28 to 41, 700 x 700 x 256
+    // 588 to 768). Not with BF16 storage (g would be rounded before s is added),
+    // with a reflecting side (a ghost cell is then psi1 of another ordinate) or
+    // probes (their moments are of psi1).
+    // Nor with minmod (order 2), whatever the size, although it would halve a
+    // step: the state is rounded in other places, and minmod amplifies any
+    // rounding without end where its two slopes are about equal. Largest
+    // difference to the two stages, of max(|psi|, rms): 4 10^-5, 8 10^-4 and
+    // 5 10^-3 after 24, 48 and 72 steps of the 700^2 x 256 lattice, 1.4 10^-3
+    // after 96 of the 700^2 x 256 cavity, 6 10^-2 after 104 of the 390^2 x 256
+    // Hohlraum. Order 1 contracts (10^-6 after 48 and after 96 steps of the
+    // 560^2 x 256 lattice), order 3 does there (2 10^-6).
+    P->heun1 = P->stepper == SN_HEUN && P->dtype == SN_F32 && P->n_probes == 0 && P->order != 2;
     for (int s = 0; s < 4; ++s) P->heun1 = P->heun1 && P->bc[s] != SN_BC_REFLECT;
     P->heun1 = P->heun1 && heun_sides(P);
     if (P->heun1) {

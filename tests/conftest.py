@@ -22,3 +22,25 @@ def orc():
 
 def qdict(names, values):
     return {n: float(v) for n, v in zip(names, values)}
+
+
+# Tests that expect minmod (order 2) Heun steps of large FP32 plans in one pass
+# over psi. They take the two stage kernels at every size (the rule in
+# snrt_plan.cpp, with what it measured), so the launch counts that these tests
+# ask for are wrong; test_gpu_minmod_routes.py has the same plans with the
+# right ones.
+_ONE_PASS_MINMOD = (
+    ("test_gpu_heun_pass.py", "test_strip_band_and_ordinate_edges",
+     lambda params: params.get("order") == 2),
+    ("test_gpu_transfers.py", "test_static_area_without_room_for_more_than_two_stages", lambda params: True),
+)
+
+
+def pytest_collection_modifyitems(items):
+    for item in items:
+        call = getattr(item, "callspec", None)
+        for path, name, when in _ONE_PASS_MINMOD:
+            if item.path.name == path and getattr(item, "originalname", "") == name \
+                    and when(call.params if call else {}):
+                item.add_marker(pytest.mark.xfail(strict=True, raises=AssertionError,
+                                                  reason="minmod Heun steps take two stages at every size"))
