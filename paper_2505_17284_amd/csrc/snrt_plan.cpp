@@ -225,17 +225,20 @@ void default_shape(const sn_plan* P, int* group_size, int* group_size_avg, int* 
         // unit: the 700^2 lattice 1.9-6% faster at 64 to 256 ordinates,
         // 560^2 and 400^2 1.3-2%; the 700^2 x 256 benchmark lattice 0.525 ->
         // 0.515 ms per step).
-        // Euler's stage, re-timed on 64^2 to 560^2 (32 to 256 ordinates), wants
-        // 500, and down to 2 ordinates per group while that makes at most 16
+        // First-order Euler, re-timed on 64^2 to 560^2 (32 to 256 ordinates),
+        // wants 500, and down to 2 ordinates per group while that makes at most 16
         // groups (more partials cost the finalize more than the shorter march
         // saves): 70^2 x 32 13.2 -> 9.8 us a step, 104^2 x 64 13.3 -> 11.3 (2 per
-        // group: 15.2), 280^2 x 128 36.3 -> 31.5. Order 3 marches longer and
-        // wants 1000: 280^2 x 128 70.6 -> 52.2, 333^2 x 128 69.9 -> 54.5.
+        // group: 15.2), 280^2 x 128 36.3 -> 31.5. Orders 2 and 3 would gain as
+        // much, but other groups round the scalar flux otherwise, and Euler with
+        // their limiters amplifies that without end (largest difference of psi,
+        // of max(|psi|, rms): 200^2 x 64 lattice 1.2 10^-3 after 144 steps, 208^2 x
+        // 64 Hohlraum 1.5 10^-3 after 96 and 7.6 10^-3 after 144).
         int gs = std::min(P->M, 32);
         auto groups = [&](int g) { return (long)(P->M + g - 1) / g; };
-        const bool euler = P->stepper == SN_EULER;
-        const long enough = !euler ? 400 : P->order == 3 ? 1000 : 500;
-        while (gs > (euler ? 2 : 8) && tiles * groups(gs) < enough && (gs > 8 || groups((gs + 1) / 2) <= 16))
+        const bool small = P->stepper == SN_EULER && P->order == 1;
+        while (gs > (small ? 2 : 8) && tiles * groups(gs) < (small ? 500 : 400) &&
+               (gs > 8 || groups((gs + 1) / 2) <= 16))
             gs = (gs + 1) / 2;
         if (gs == 32 && P->order < 3) {  // order 3 (bound by its arithmetic) not re-timed
             const long wg = tiles * groups(gs);

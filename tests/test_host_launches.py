@@ -51,3 +51,15 @@ def test_minmod_heun_steps_are_two_stages_at_every_size(workdir, kind, n, M):
 def test_heun_steps_of_orders_1_and_3_are_one_pass(workdir, order):
     got = _on_host(workdir, _kernels_of_steps, "lattice", 70, 32, order, 1, 2)
     assert got == ["sn_heun_kernel", "sn_heun_finalize_kernel"] * 2 + ["sn_materialize_kernel"]
+
+
+@pytest.mark.parametrize("order", [2, 3])
+@pytest.mark.parametrize("n,M", [(70, 32), (104, 64), (140, 64), (200, 64), (208, 64), (280, 128), (333, 128), (560, 256)])
+def test_euler_groups_of_limited_orders_are_those_of_the_update_stage(n, M, order):
+    """The grouping decides how phi is rounded, and the limited orders amplify
+    that: Euler keeps the groups of Heun's update stage there."""
+    from paper_2505_17284_amd import inputs as I
+    from paper_2505_17284_amd import solver
+
+    a, b = (solver.plan_info(I.lattice(n, M, order=order, stepper=s)) for s in (I.EULER, I.HEUN))
+    assert a["group_size"] == b["group_size"]
