@@ -479,7 +479,8 @@ bool heun_sides(sn_plan* P) {
                     st.n++;
                 }
             }
-            st.full = st.n > 0 || tx == 0 || tx == P->hntx - 1 ? 1 : 0;
+            // also where the halo reaches the grid's last columns: a last strip of up to 8
+            st.full = st.n > 0 || tx == 0 || (tx + 1) * kStripX + kStripLead > P->nx ? 1 : 0;
             P->hsides = std::max(P->hsides, st.n);
             P->hstrip_h.push_back(st);
         }
