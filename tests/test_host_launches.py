@@ -63,3 +63,24 @@ def test_euler_groups_of_limited_orders_are_those_of_the_update_stage(n, M, orde
 
     a, b = (solver.plan_info(I.lattice(n, M, order=order, stepper=s)) for s in (I.EULER, I.HEUN))
     assert a["group_size"] == b["group_size"]
+
+
+def _threads_of_init(host, nx, M, order, stepper):
+    quad = I.tessellation_quadrature(22) if M == 1936 else None  # noqa: F821
+    p = I.lattice(nx, 32 if quad else M, order=order, stepper=stepper, quad=quad)  # noqa: F821
+    h = host.plan(p, bind=False)
+    host.L.check(host.bind(h), "bind")
+    host.launches()
+    host.L.check(host.lib.sn_plan_init(h, *host.addresses(4 * p.M * p.ny * p.nx), None), "init")
+    host.L.check(host.lib.sn_plan_run(h, 1, None), "run")
+    return [p.M * p.ny * p.nx, host.launches()]
+
+
+@pytest.mark.parametrize("nx,M,order,stepper", [(700, 256, 2, 1), (1500, 1936, 1, 0), (1500, 1936, 3, 1)])
+def test_launches_of_large_states_stay_below_2_32_threads(workdir, nx, M, order, stepper):
+    """HIP takes fewer than 2^32 threads per launch; 1500^2 x 1936 has 4.4e9
+    cell-ordinates, and psi0 is unpacked a thread each."""
+    n, launches = _on_host(workdir, _threads_of_init, nx, M, order, stepper)
+    assert all(blocks * threads < 2 ** 32 for _, blocks, threads in launches), launches
+    unpacked = [blocks * threads for k, blocks, threads in launches if k == "sn_pack_kernel"]
+    assert n <= sum(unpacked) < n + 256 * len(unpacked) and len(unpacked) <= 1 + n // 2 ** 31
