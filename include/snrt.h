@@ -254,7 +254,10 @@ sn_status sn_plan_bind_static(sn_plan *plan, void *psi_a, void *psi_b);
  * Asynchronous on `stream`; psi0 is copied before the call returns. */
 sn_status sn_plan_init(sn_plan *plan, const float *psi0, void *stream);
 
-/* Advance min(n_steps, N_t - step) time steps. Asynchronous. */
+/* Advance min(n_steps, N_t - step) time steps. Asynchronous. Where a run
+ * fails between two steps that each take one pass over psi, the state is
+ * unfinished: sn_plan_qoi, sn_plan_read_psi and sn_batch_admit return
+ * SN_ERR_STATE until another run (of 0 steps, if need be) or sn_plan_init. */
 sn_status sn_plan_run(sn_plan *plan, int32_t n_steps, void *stream);
 
 /* Advance exactly n_steps (may go past N_t; used for timing). Asynchronous. */

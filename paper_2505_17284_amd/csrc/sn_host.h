@@ -107,7 +107,7 @@ struct sn_plan {
     bool bound = false, inited = false;
     int64_t step = 0;
     int cur = 0;  // buffer holding the current state
-    bool shifted = false;  // during a run of one-pass steps: psi[cur] lacks the shift plane
+    bool shifted = false;  // during a run of one-pass steps, and after one that failed: psi[cur] lacks the shift plane
 
     // timing
     bool timing = false;
@@ -147,6 +147,8 @@ snk::HeunFinArgs heun_fin_args(const sn_plan* P);
 snk::MaterializeArgs materialize_args(const sn_plan* P, const char* in, char* out);
 // Workgroups of that finalize.
 int finalize_workgroups(const sn_plan* P, int kind);
+// SN_ERR_STATE while P's state lacks its shift (a run of one-pass steps failed).
+sn_status whole_state(const sn_plan* P);
 // Issue n whole steps of P on s with plain launches (no graph, no timing);
 // advances P's step counter and buffer parity. Used by a batch for plans
 // that fill the GPU on their own.

@@ -179,6 +179,8 @@ sn_status sn_batch_admit(sn_batch* B, sn_plan* P, int32_t* slot) {
     *slot = -1;
     if (!P->bound || !P->inited) return fail(SN_ERR_STATE, "plan not bound and initialised");
     if (P->batch) return fail(SN_ERR_STATE, "plan is already admitted to a batch");
+    const sn_status whole = whole_state(P);
+    if (whole != SN_OK) return whole;
     if (P->order != B->o.order || P->stepper != B->o.stepper || P->dtype != B->o.psi_dtype)
         return fail(SN_ERR_INVALID, "plan (order %d, stepper %d, dtype %d) does not match the batch (%d, %d, %d)",
                     P->order, P->stepper, P->dtype, B->o.order, B->o.stepper, B->o.psi_dtype);

@@ -1109,7 +1109,7 @@ sn_status capture_steps(sn_plan* P, int e) {
 sn_status run_steps(sn_plan* P, int n, hipStream_t s) {
     if (!P->bound || !P->inited) return fail(SN_ERR_STATE, "plan not bound and initialised");
     if (P->batch) return fail(SN_ERR_STATE, "plan is admitted to a batch; the batch advances it");
-    if (n <= 0) return SN_OK;
+    if (n <= 0 && !P->shifted) return SN_OK;  // shifted: a run before failed; this one goes on from there and settles
     int done = 0;
     if (P->graph_steps > 0 && !P->timing) {
         const int K = P->graph_steps;
@@ -1135,6 +1135,11 @@ sn_status run_steps(sn_plan* P, int n, hipStream_t s) {
 }
 
 }  // namespace
+
+sn_status snh::whole_state(const sn_plan* P) {
+    if (!P->shifted) return SN_OK;
+    return fail(SN_ERR_STATE, "the last run failed between two steps: run on (0 steps will do) or initialise the plan");
+}
 
 sn_status snh::issue_steps(sn_plan* P, int n, hipStream_t s) { return launch_steps(P, n, s, false); }
 
@@ -1376,7 +1381,8 @@ sn_status sn_plan_qoi(sn_plan* P, sn_qoi* out, void* stream) {
     if (!P || !out) return fail(SN_ERR_INVALID, "NULL argument");
     if (!P->bound || !P->inited) return fail(SN_ERR_STATE, "plan not bound and initialised");
     hipStream_t s = (hipStream_t)stream;
-    sn_status st = launch_stage_pair(P, -1, s, false);
+    sn_status st = whole_state(P);
+    if (st == SN_OK) st = launch_stage_pair(P, -1, s, false);
     if (st != SN_OK) return st;
     // off_inst .. off_flags in one copy
     char buf[2 * align256(kMaxQ * sizeof(double)) + align256(sizeof(double)) + sizeof(int32_t)];
@@ -1428,6 +1434,8 @@ sn_status sn_plan_qoi(sn_plan* P, sn_qoi* out, void* stream) {
 sn_status sn_plan_read_psi(const sn_plan* P, float* host_out, void* stream) {
     if (!P || !host_out) return fail(SN_ERR_INVALID, "NULL argument");
     if (!P->bound || !P->inited) return fail(SN_ERR_STATE, "plan not bound and initialised");
+    const sn_status whole = whole_state(P);
+    if (whole != SN_OK) return whole;
     hipStream_t s = (hipStream_t)stream;
     const size_t cells = (size_t)P->ny * P->nx;
     std::vector<uint16_t> tmp;

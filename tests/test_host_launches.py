@@ -84,3 +84,44 @@ def test_launches_of_large_states_stay_below_2_32_threads(workdir, nx, M, order,
     assert all(blocks * threads < 2 ** 32 for _, blocks, threads in launches), launches
     unpacked = [blocks * threads for k, blocks, threads in launches if k == "sn_pack_kernel"]
     assert n <= sum(unpacked) < n + 256 * len(unpacked) and len(unpacked) <= 1 + n // 2 ** 31
+
+
+def _reads_after_a_failed_run(host, order, graph, function, k):
+    p = I.lattice(70, 32, order=order, stepper=I.HEUN)  # noqa: F821
+    h = host.plan(p)
+    if graph:
+        host.L.check(host.lib.sn_plan_use_graph(h, graph), "graph")
+    host.launches()
+    host.fail(function, k)
+    out = dict(run=host.lib.sn_plan_run(h, 7, None), replays=host.stub.stub_graph_replays())
+    host.launches()
+    psi, q = host.addresses(1 << 26)[0], host.L.SnQoi()
+
+    def reads():
+        import numpy as np
+        a = np.zeros((p.M, p.ny, p.nx), np.float32)
+        st = host.lib.sn_plan_qoi(h, host.L.ctypes.byref(q), None)
+        return [host.lib.sn_plan_read_psi(h, a.ctypes.data, None), host.L.SN_OK if st == host.L.SN_ERR_NONFINITE else st]
+
+    out["reads"] = reads()
+    host.fail("", 0)
+    out["settle"] = host.lib.sn_plan_run(h, 0, None)
+    out["launches_then"] = [n for n, _, _ in host.launches()]
+    out["reads_then"] = reads()
+    return out
+
+
+@pytest.mark.parametrize("graph,function,k", [(0, "hipLaunchKernel", k) for k in (1, 2, 3, 4, 9, 14, 15)]
+                         + [(2, "hipGraphInstantiate", 1), (2, "hipGraphInstantiate", 2), (2, "hipGraphLaunch", 1),
+                            (2, "hipGraphLaunch", 3), (2, "hipStreamEndCapture", 2)])
+def test_a_run_that_fails_between_one_pass_steps_is_not_read_as_if_it_had_ended(workdir, graph, function, k):
+    """After a step the buffer lacks the step's shift until the run's end adds
+    it: a run that ends before has SN_ERR_STATE for readers until the state is
+    settled (any run, also of no steps, does)."""
+    r = _on_host(workdir, _reads_after_a_failed_run, 3, graph, function, k)
+    assert r["run"] == 3  # SN_ERR_DEVICE
+    steps = (k - 1) // 2 if not graph else r["replays"]
+    ok, state = 0, 7
+    assert r["reads"] == ([state, state] if steps > 0 else [ok, ok])
+    assert r["settle"] == ok and r["reads_then"] == [ok, ok]
+    assert r["launches_then"].count("sn_materialize_kernel") == (1 if steps > 0 else 0)
