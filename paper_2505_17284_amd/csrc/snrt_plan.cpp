@@ -1320,7 +1320,7 @@ sn_status sn_plan_init(sn_plan* P, const float* psi0, void* stream) {
         HIP_TRY(hipMemcpyAsync(P->psi[1], src, n * P->elem, hipMemcpyHostToDevice, s), "upload psi0");
         // a thread per element, and HIP takes fewer than 2^32 per launch: planes in turn
         const int64_t cells = (int64_t)P->ny * P->nx;
-        const int most = (int)std::max<int64_t>(1, (int64_t(1) << 31) / cells);
+        const int most = (int)std::min<int64_t>(P->M, std::max<int64_t>(1, (int64_t(1) << 31) / cells));
         for (int k = 0; k < P->M; k += most)
             HIP_TRY(launch_pack(P->dtype, pack_args(P, P->psi[0] + k * P->plane * P->elem, P->psi[1] + k * cells * P->elem,
                                                     std::min(most, P->M - k)), false, s), "unpack psi0");

@@ -76,7 +76,7 @@ def _threads_of_init(host, nx, M, order, stepper):
     return [p.M * p.ny * p.nx, host.launches()]
 
 
-@pytest.mark.parametrize("nx,M,order,stepper", [(700, 256, 2, 1), (1500, 1936, 1, 0), (1500, 1936, 3, 1)])
+@pytest.mark.parametrize("nx,M,order,stepper", [(7, 32, 2, 1), (700, 256, 2, 1), (1500, 1936, 1, 0), (1500, 1936, 3, 1)])
 def test_launches_of_large_states_stay_below_2_32_threads(workdir, nx, M, order, stepper):
     """HIP takes fewer than 2^32 threads per launch; 1500^2 x 1936 has 4.4e9
     cell-ordinates, and psi0 is unpacked a thread each."""
@@ -84,6 +84,21 @@ def test_launches_of_large_states_stay_below_2_32_threads(workdir, nx, M, order,
     assert all(blocks * threads < 2 ** 32 for _, blocks, threads in launches), launches
     unpacked = [blocks * threads for k, blocks, threads in launches if k == "sn_pack_kernel"]
     assert n <= sum(unpacked) < n + 256 * len(unpacked) and len(unpacked) <= 1 + n // 2 ** 31
+
+
+def _launches_of_one_cell(host, nx, ny):
+    p = I.random_materials(nx, ny, 1, seed=1, M=32, order=1, rects=[])  # noqa: F821
+    h = host.plan(p, bind=False)
+    host.L.check(host.bind(h), "bind")
+    host.launches()
+    host.L.check(host.lib.sn_plan_init(h, *host.addresses(4 * p.M * nx * ny), None), "init")
+    return host.launches()
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 1), (1, 3)])
+def test_psi0_of_the_smallest_grids_is_unpacked_once(workdir, nx, ny):
+    unpacked = [b * t for k, b, t in _on_host(workdir, _launches_of_one_cell, nx, ny) if k == "sn_pack_kernel"]
+    assert unpacked == [256]
 
 
 def _reads_after_a_failed_run(host, order, graph, function, k):
