@@ -207,7 +207,10 @@ sn_status sn_plan_create(const sn_problem *problem, sn_plan **out);
 /* Same, with an explicit launch shape (0 = library default for each):
  * group_size ordinates per workgroup (both stages), rows_per_wave grid rows
  * per wavefront (2 or 4), waves_per_group compute wavefronts per workgroup
- * (4 or 8; one more wavefront stages rows for them). Returns
+ * (4 or 8; one more wavefront stages rows for them). The shape is the stage
+ * kernels': a plan with a group size takes its Heun steps as two stages, also
+ * where the library would take one pass over psi; rows and waves alone leave
+ * that choice, and shape a one-pass plan's QoI pass only. Returns
  * SN_ERR_UNSUPPORTED for a shape the library was not compiled for. */
 sn_status sn_plan_create_tuned(const sn_problem *problem, int32_t group_size,
                                int32_t rows_per_wave, int32_t waves_per_group,
@@ -330,7 +333,8 @@ sn_status sn_plan_use_graph(sn_plan *plan, int32_t steps_per_graph);
  * milliseconds and launch counts per kernel kind: index 0 = Euler stage,
  * 1 = Heun stage 1, 2 = Heun stage 2, 3 = QoI finalize. Plans that take a
  * Heun step in one pass over psi (FP32, orders 1 and 3, no reflecting side, no
- * probes; the library's choice) count it under 2, and nothing under 1.
+ * probes, no group size asked for; the library's choice) count it under 2, and
+ * nothing under 1.
  * Synchronises. */
 sn_status sn_plan_set_timing(sn_plan *plan, int32_t on);
 sn_status sn_plan_kernel_ms(sn_plan *plan, double ms[4], int64_t counts[4]);

@@ -641,7 +641,10 @@ sn_status derive(sn_plan* P, int group_size, int group_size_avg, int rows, int w
     // after 96 of the 700^2 x 256 cavity, 6 10^-2 after 104 of the 390^2 x 256
     // Hohlraum. Order 1 contracts (10^-6 after 48 and after 96 steps of the
     // 560^2 x 256 lattice), order 3 does there (2 10^-6).
-    P->heun1 = P->stepper == SN_HEUN && P->dtype == SN_F32 && P->n_probes == 0 && P->order != 2;
+    // Nor where the caller asks for ordinate groups: those are the stage kernels'.
+    // (Rows and waves alone do not count: every member of a batch names them.)
+    const bool grouped = group_size > 0 || group_size_avg > 0;
+    P->heun1 = P->stepper == SN_HEUN && P->dtype == SN_F32 && P->n_probes == 0 && P->order != 2 && !grouped;
     for (int s = 0; s < 4; ++s) P->heun1 = P->heun1 && P->bc[s] != SN_BC_REFLECT;
     P->heun1 = P->heun1 && heun_sides(P);
     if (P->heun1) {

@@ -221,22 +221,28 @@ TUNE_CANDIDATES = ((0, 0), (8, 8), (16, 16), (32, 16), (32, 32), (64, 32), (64, 
 
 def autotune(problem, candidates=TUNE_CANDIDATES, steps: int = 4, reps: int = 2, device: str = "cuda:0") -> dict:
     """The fastest ordinate-group sizes for the problem's shape class (grid,
-    ordinates, order, stepper, storage), measured on the device: for every
-    distinct effective candidate, the best of `reps` wall-clock timings of
-    `steps` whole steps (stages, finalizes, launches) after one warm-up step.
-    Cached per class for the life of the process; returns group_size,
-    group_size_average and the measured ms per step."""
+    ordinates, order, stepper, storage, and whether it takes Heun steps in one
+    pass), measured on the device: for every distinct effective candidate, the
+    best of `reps` wall-clock timings of `steps` whole steps (stages, finalizes,
+    launches) after one warm-up step. One-pass steps have no groups to choose:
+    0 (the library's default) and its time. Cached per class for the life of the
+    process; returns group_size, group_size_average and the measured ms per step."""
     import time
 
     torch = _torch()
-    key = (problem.nx, problem.ny, problem.M, problem.order, problem.stepper, problem.psi_dtype)
+    info = plan_info(problem)
+    default = (info["group_size"], info["group_size_average"])
+    # naming the default's groups makes it two stages, whose scratch is smaller
+    one_pass = info["scratch_bytes"] != plan_info(problem, group_size=default[0],
+                                                  group_size_average=default[1])["scratch_bytes"]
+    key = (problem.nx, problem.ny, problem.M, problem.order, problem.stepper, problem.psi_dtype, one_pass)
     if key in _TUNED:
         return _TUNED[key]
     best = None
     seen = set()
-    for gs, gsa in candidates:
+    for gs, gsa in ((0, 0),) if one_pass else candidates:
         info = plan_info(problem, group_size=gs, group_size_average=gsa or gs)
-        eff = (info["group_size"], info["group_size_average"])
+        eff = (0, 0) if one_pass else (info["group_size"], info["group_size_average"])
         if eff in seen:
             continue
         seen.add(eff)

@@ -140,3 +140,23 @@ def test_a_run_that_fails_between_one_pass_steps_is_not_read_as_if_it_had_ended(
     assert r["reads"] == ([state, state] if steps > 0 else [ok, ok])
     assert r["settle"] == ok and r["reads_then"] == [ok, ok]
     assert r["launches_then"].count("sn_materialize_kernel") == (1 if steps > 0 else 0)
+
+
+def _kernels_of_shaped_steps(host, order, shape):
+    h = host.plan(I.lattice(140, 64, order=order, stepper=I.HEUN), **shape)  # noqa: F821
+    host.launches()
+    host.L.check(host.lib.sn_plan_run(h, 2, None), "run")
+    return [k for k, _, _ in host.launches()]
+
+
+@pytest.mark.parametrize("order", [1, 2, 3])
+@pytest.mark.parametrize("shape", [dict(group_size=8), dict(group_size_average=16), dict(group_size=5, rows=4, waves=8)])
+def test_ordinate_groups_asked_for_shape_the_steps(workdir, order, shape):
+    assert _on_host(workdir, _kernels_of_shaped_steps, order, shape) == TWO_STAGES * 2
+
+
+@pytest.mark.parametrize("order", [1, 3])
+def test_rows_and_waves_alone_leave_the_choice(workdir, order):
+    """Batches name them for every member, whose steps are those of the plan alone."""
+    got = _on_host(workdir, _kernels_of_shaped_steps, order, dict(rows=2, waves=4))
+    assert got[:2] == ["sn_heun_kernel", "sn_heun_finalize_kernel"]
