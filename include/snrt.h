@@ -238,8 +238,12 @@ sn_status sn_plan_bind(sn_plan *plan, void *psi_a, void *psi_b, void *scratch);
  * caller's, as for sn_plan_bind. The area belongs to the device current at
  * this call. Allocates nothing: no device allocation or free, and no
  * allocating library routine.
- *  - SN_ERR_UNSUPPORTED when the plan's scratch_bytes (sn_plan_get_info)
- *    exceed SN_STATIC_SCRATCH_BYTES: bind caller-owned scratch instead.
+ *  - A plan whose scratch_bytes (sn_plan_get_info) exceed
+ *    SN_STATIC_SCRATCH_BYTES only for the areas of one-pass Heun steps and of
+ *    packed reads does without them while it is bound here: its steps take two
+ *    stages, phi and psi are read row by row.
+ *  - SN_ERR_UNSUPPORTED when the rest exceeds SN_STATIC_SCRATCH_BYTES: bind
+ *    caller-owned scratch instead.
  *  - SN_ERR_BUSY while another plan is bound to the same device's area: the
  *    area holds one plan's tables, QoI accumulators and phi at a time; that
  *    plan must be destroyed or bound elsewhere first. The area keeps what the

@@ -63,6 +63,7 @@ struct sn_plan {
     size_t elem = 4, psi_bytes = 0, scratch_bytes = 0;
     size_t plain_scratch_bytes = 0;  // without the one-pass Heun step's areas (heun1) and the packed plane (packs)
     size_t clear_end = 0;            // off_phi .. clear_end starts from zero
+    bool plain = false;              // bound to scratch without those areas: two stages, planes read row by row
     bool packs = false;              // off_pack: one plane's interior, compact
     size_t off_pack = 0;
     mutable std::mutex pack_mu;      // held by a reading call until its copies have ended
@@ -87,8 +88,9 @@ struct sn_plan {
     std::vector<int32_t> ftile_h;  // [ntiles][3]: first entry, entries per lane, lanes
     int face_lds = 0;              // bytes of the largest table read from LDS (more than kFaceRegs per lane)
     size_t off_fent = 0, off_ftile = 0;
-    // Heun steps as one pass over psi (sn_heun_impl.h), where the statement allows it
-    bool heun1 = false;
+    // Heun steps as one pass over psi (sn_heun_impl.h), where the statement
+    // (one_pass) and the scratch that the plan is bound to allow it
+    bool one_pass = false, heun1 = false;
     int hwaves = 1, hband = 1, hnbands = 1, hntx = 1, hG = 0, hn_wg = 0, hcell_wg = 0, hsides = 0, hslices = 1;
     float wsum = 0;
     std::vector<snk::OrdConst> hord_h;  // sorted by quadrant
@@ -154,8 +156,9 @@ sn_status whole_state(const sn_plan* P);
 // that fill the GPU on their own.
 sn_status issue_steps(sn_plan* P, int n, hipStream_t s);
 // Validate and lend buffers to P (the body of sn_plan_bind, without touching
-// a static-scratch binding; P->static_dev becomes -1 on success).
-sn_status bind_buffers(sn_plan* P, void* psi_a, void* psi_b, void* scratch);
+// a static-scratch binding; P->static_dev becomes -1 on success). plain: the
+// scratch holds plain_scratch_bytes only.
+sn_status bind_buffers(sn_plan* P, void* psi_a, void* psi_b, void* scratch, bool plain);
 // P no longer holds the library-held scratch area of device dev (snrt_static.hip).
 void release_static_scratch(const sn_plan* P, int dev);
 

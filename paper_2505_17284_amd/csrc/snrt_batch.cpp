@@ -58,7 +58,9 @@ struct sn_batch {
 
 namespace {
 
-uint64_t footprint(const sn_plan* P) { return 2 * (uint64_t)P->psi_bytes + (uint64_t)P->scratch_bytes; }
+uint64_t footprint(const sn_plan* P) {
+    return 2 * (uint64_t)P->psi_bytes + (uint64_t)(P->plain ? P->plain_scratch_bytes : P->scratch_bytes);
+}
 
 sn_status check_opts(const sn_batch_opts* o) {
     if (!o) return fail(SN_ERR_INVALID, "opts is NULL");

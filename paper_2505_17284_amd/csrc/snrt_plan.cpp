@@ -717,6 +717,7 @@ sn_status derive(sn_plan* P, int group_size, int group_size_avg, int rows, int w
         put(P->off_hstrip, P->hstrip_h);
         put(P->off_hside, P->hside_h);
     }
+    P->one_pass = P->heun1;
     P->packs = true;
     take(&P->off_pack, (size_t)P->nx * P->ny * sizeof(float));
     P->scratch_bytes = off;
@@ -1146,19 +1147,24 @@ sn_status snh::whole_state(const sn_plan* P) {
 
 sn_status snh::issue_steps(sn_plan* P, int n, hipStream_t s) { return launch_steps(P, n, s, false); }
 
-sn_status snh::bind_buffers(sn_plan* P, void* psi_a, void* psi_b, void* scratch) {
+sn_status snh::bind_buffers(sn_plan* P, void* psi_a, void* psi_b, void* scratch, bool plain) {
     if (!P || !psi_a || !psi_b || !scratch) return fail(SN_ERR_INVALID, "NULL argument");
     if (P->batch) return fail(SN_ERR_STATE, "plan is admitted to a batch");
     const uintptr_t pa = (uintptr_t)psi_a, pb = (uintptr_t)psi_b, ps = (uintptr_t)scratch;
     if ((pa | pb | ps) & 255) return fail(SN_ERR_INVALID, "device buffers must be 256-byte aligned");
     auto overlap = [](uintptr_t a, size_t na, uintptr_t b, size_t nb) { return a < b + nb && b < a + na; };
-    if (overlap(pa, P->psi_bytes, pb, P->psi_bytes) || overlap(pa, P->psi_bytes, ps, P->scratch_bytes) ||
-        overlap(pb, P->psi_bytes, ps, P->scratch_bytes))
+    const size_t ns = plain ? P->plain_scratch_bytes : P->scratch_bytes;
+    if (overlap(pa, P->psi_bytes, pb, P->psi_bytes) || overlap(pa, P->psi_bytes, ps, ns) ||
+        overlap(pb, P->psi_bytes, ps, ns))
         return fail(SN_ERR_INVALID, "device buffers overlap");
     drop_graph(P);
     P->psi[0] = (char*)psi_a;
     P->psi[1] = (char*)psi_b;
     P->scratch = (char*)scratch;
+    P->plain = plain;
+    P->heun1 = P->one_pass && !plain;
+    P->packs = !plain;
+    P->shifted = false;
     P->static_dev = -1;
     P->bound = true;
     P->inited = false;
@@ -1275,7 +1281,7 @@ sn_status sn_plan_get_info(const sn_plan* P, sn_plan_info* out) {
 sn_status sn_plan_bind(sn_plan* P, void* psi_a, void* psi_b, void* scratch) {
     if (!P) return fail(SN_ERR_INVALID, "NULL argument");
     const int old_dev = P->static_dev;
-    const sn_status st = snh::bind_buffers(P, psi_a, psi_b, scratch);
+    const sn_status st = snh::bind_buffers(P, psi_a, psi_b, scratch, false);
     if (st == SN_OK && old_dev >= 0) snh::release_static_scratch(P, old_dev);
     return st;
 }

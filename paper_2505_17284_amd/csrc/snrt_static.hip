@@ -63,14 +63,8 @@ extern "C" sn_status sn_plan_bind_static(sn_plan* P, void* psi_a, void* psi_b) {
         g_ptr[dev] = p;
     }
     const int old_dev = P->static_dev;
-    const size_t whole = P->scratch_bytes;
-    if (plain) P->scratch_bytes = P->plain_scratch_bytes;
-    const sn_status st = snh::bind_buffers(P, psi_a, psi_b, g_ptr[dev]);
-    if (st != SN_OK) {
-        P->scratch_bytes = whole;
-        return st;
-    }
-    if (plain) P->heun1 = P->packs = false;
+    const sn_status st = snh::bind_buffers(P, psi_a, psi_b, g_ptr[dev], plain);
+    if (st != SN_OK) return st;
     if (old_dev >= 0 && old_dev < kMaxDevices && old_dev != dev && g_owner[old_dev] == P) g_owner[old_dev] = nullptr;
     g_owner[dev] = P;
     P->static_dev = dev;

@@ -160,3 +160,30 @@ def test_rows_and_waves_alone_leave_the_choice(workdir, order):
     """Batches name them for every member, whose steps are those of the plan alone."""
     got = _on_host(workdir, _kernels_of_shaped_steps, order, dict(rows=2, waves=4))
     assert got[:2] == ["sn_heun_kernel", "sn_heun_finalize_kernel"]
+
+
+def _bound_twice(host):
+    p = I.lattice(700, 256, order=3, stepper=I.HEUN)  # noqa: F821
+    h = host.plan(p, bind=False)
+    out, phi = [], host.addresses(1 << 23)[0]
+    info = host.info(h)
+    for static in (False, True, False):
+        bind = (host.lib.sn_plan_bind_static(h, *host.addresses(info["psi_bytes"], info["psi_bytes"])) if static
+                else host.bind(h))
+        host.L.check(bind, "bind")
+        host.L.check(host.lib.sn_plan_init(h, None, None), "init")
+        host.launches()
+        host.L.check(host.lib.sn_plan_run(h, 2, None), "run")
+        host.L.check(host.lib.sn_plan_read_phi(h, phi, None), "phi")
+        out.append([host.info(h)["scratch_bytes"], [k for k, _, _ in host.launches()]])
+    return out
+
+
+def test_a_plan_bound_to_the_static_area_and_then_to_caller_scratch(workdir):
+    """The static area holds this plan only without the one-pass areas and the
+    packed plane; scratch of the size sn_plan_get_info asks for has them again."""
+    first, static, then = _on_host(workdir, _bound_twice)
+    assert first[0] > 64 << 20 and static[0] == then[0] == first[0]
+    assert static[1] == TWO_STAGES * 2
+    assert then[1] == first[1] == ["sn_heun_kernel", "sn_heun_finalize_kernel"] * 2 + ["sn_materialize_kernel",
+                                                                                        "sn_pack_kernel"]
