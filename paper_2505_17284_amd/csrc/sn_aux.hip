@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(256) sn_ghost_fill_kernel(const GhostArgs a) {
 // into the time integral by one thread. The order of every sum is fixed, so
 // the result does not depend on which chunk finishes last.
 // Workgroups [nq q_split, + n_phi_wg): phi = sum over groups of the stage's
-// partial scalar fluxes, in group order, for every interior cell (4 padded
+// partial scalar fluxes, in group order (wide: in FP64), for every interior cell (4 padded
 // columns per thread, ny * pitch / 4 threads), first adding the replaced phi
 // (the stage input's) to the fluence when that is kept. The QoI slots of the
 // space-time probes also accumulate into the window of the current step.
@@ -136,6 +136,22 @@ __device__ __forceinline__ void finish_slot(FArgs a, int s, double sum, double s
     }
 }
 
+// The groups' partial scalar fluxes, in group order: the first 16 from part, the
+// others from memory.
+template <typename F>
+__device__ __forceinline__ float4 sum_planes(FArgs a, const float4 (&part)[16], int64_t off) {
+    const int G = a.G;
+    F x = part[0].x, y = part[0].y, z = part[0].z, w = part[0].w;
+#pragma unroll
+    for (int g = 1; g < 16; ++g)
+        if (g < G) x += part[g].x, y += part[g].y, z += part[g].z, w += part[g].w;
+    for (int g = 16; g < G; ++g) {
+        const float4 p = *reinterpret_cast<const float4*>(a.phi_part + (int64_t)g * a.plane + off);
+        x += p.x, y += p.y, z += p.z, w += p.w;
+    }
+    return make_float4((float)x, (float)y, (float)z, (float)w);
+}
+
 __device__ __forceinline__ void finalize_block(FArgs a, int blk) {
     const int nqb = a.nq * a.q_split;
     if (blk >= nqb) {
@@ -151,23 +167,7 @@ __device__ __forceinline__ void finalize_block(FArgs a, int blk) {
 #pragma unroll
         for (int g = 0; g < 16; ++g)
             if (g < G) part[g] = *reinterpret_cast<const float4*>(a.phi_part + (int64_t)g * a.plane + off);
-        float4 acc = part[0];
-#pragma unroll
-        for (int g = 1; g < 16; ++g) {
-            if (g < G) {
-                acc.x += part[g].x;
-                acc.y += part[g].y;
-                acc.z += part[g].z;
-                acc.w += part[g].w;
-            }
-        }
-        for (int g = 16; g < G; ++g) {
-            const float4 p = *reinterpret_cast<const float4*>(a.phi_part + (int64_t)g * a.plane + off);
-            acc.x += p.x;
-            acc.y += p.y;
-            acc.z += p.z;
-            acc.w += p.w;
-        }
+        const float4 acc = a.wide ? sum_planes<double>(a, part, off) : sum_planes<float>(a, part, off);
         const int i0 = 4 * c4 - a.ox;  // interior column of the first of the four
         if (a.fluence != nullptr) {
             // phi still holds the stage input's scalar flux: add its share of

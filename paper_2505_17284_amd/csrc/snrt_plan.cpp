@@ -926,6 +926,11 @@ FinalizeArgs snh::finalize_args(const sn_plan* P, int kind) {
     f.G = P->G_l[l];
     f.ox = P->ox;
     f.n_phi_wg = kind < 0 ? 0 : (int)(((int64_t)P->ny * (P->pitch / 4) + 255) / 256);
+    // First-order Euler's small groups make up to 16 partials of as little as two
+    // ordinates: summed in FP32, phi of 70^2 x 32 would be 6.5 10^-8 off (rms, of
+    // its value), more than with four groups (4.5); so, 2.4. Other plans round as
+    // they always have (their limiters amplify a change).
+    f.wide = P->stepper == SN_EULER && P->order == 1 ? 1 : 0;
     f.qpart = P->sp<double>(P->off_qpart);
     f.scale = P->sp<double>(P->off_scale);
     f.inst = P->sp<double>(P->off_inst);
