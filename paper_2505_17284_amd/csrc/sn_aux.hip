@@ -309,7 +309,7 @@ __device__ __forceinline__ void heun_finalize_block(HFArgs a, int blk, double* r
             const bool in = i0 + e >= 0 && i0 + e < a.nx;
             const RegConst r = a.reg[in ? reg4 >> (8 * e) & 0xffu : 0u];
             so[e] = (float)(0.5 * fma((double)r.cs, v1[e], (double)r.cq));
-            const double p = fma((double)a.wsum, (double)so[e], vg[e]);
+            const double p = fma(a.wsum, (double)so[e], vg[e]);
             po[e] = (float)p;
             bo[e] = (float)fma((double)r.cs, p, (double)r.cq);
             if (in) {

@@ -92,7 +92,7 @@ struct sn_plan {
     // (one_pass) and the scratch that the plan is bound to allow it
     bool one_pass = false, heun1 = false;
     int hwaves = 1, hband = 1, hnbands = 1, hntx = 1, hG = 0, hn_wg = 0, hcell_wg = 0, hsides = 0, hslices = 1;
-    float wsum = 0;
+    double wsum = 0;
     std::vector<snk::OrdConst> hord_h;  // sorted by quadrant
     std::vector<snk::HeunGroup> hgroup_h;
     std::vector<snk::HeunStrip> hstrip_h;

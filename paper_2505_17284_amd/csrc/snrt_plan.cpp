@@ -652,9 +652,8 @@ sn_status derive(sn_plan* P, int group_size, int group_size_avg, int rows, int w
         P->heun1 = heun_groups(P);
     }
     if (P->heun1) {
-        double ws = 0;
-        for (int k = 0; k < P->M; ++k) ws += P->ord_h[k].w;
-        P->wsum = (float)ws;
+        P->wsum = 0;
+        for (int k = 0; k < P->M; ++k) P->wsum += P->ord_h[k].w;
         P->hn_wg = P->hntx * P->hnbands * P->hG;
         // 16 groups or more where whole workgroups of cells would not fill the compute units
         const int64_t quads = (int64_t)P->ny * (P->pitch / 4);
