@@ -501,7 +501,10 @@ bool heun_sides(sn_plan* P) {
 // 12 rows standing for a march's start (its first loads, three rows before
 // the band) and its end, and a last round of x of the resident workgroups
 // counting 0.4 + 0.6 x: short bands fill the chip on small grids, tall ones
-// repeat less.
+// repeat less. Resident are the workgroups of 16 waves per compute unit that its
+// LDS holds (32 ordinates, 4 waves: three, not four; counted as four, 1300^2 x 32
+// took bands of 64 rows and 253 us a step at order 3, now 44 rows and 221; 700^2 x
+// 32 20 rows and 103 us, now 28 and 91).
 void heun_shape(sn_plan* P) {
     int quad[4] = {0, 0, 0, 0};
     for (int k = 0; k < P->M; ++k) quad[(P->xi[k] > 0 ? 1 : 0) + (P->eta[k] > 0 ? 2 : 0)]++;
@@ -514,7 +517,8 @@ void heun_shape(sn_plan* P) {
         if (groups > 0) waves = std::max(waves, (w + groups - 1) / groups);
     }
     P->hwaves = want;
-    const double slots = 256.0 * std::max(1, 16 / waves);
+    const int per_cu = std::min<int>(16 / waves, (int)(kLdsPerCu / heun_lds_bytes(waves, P->hsides)));
+    const double slots = (double)kCus * std::max(1, per_cu);
     double best = 0;
     P->hband = 0;
     for (int band = 4; band <= 64; band += 4) {

@@ -1,6 +1,6 @@
 /* A HIP runtime that does nothing, for host tests of libsnrt's launch
  * sequences: loaded (RTLD_GLOBAL) before the library, its functions stand in
- * for libamdhip64's. It keeps the list of launches (kernel, grid x block) and
+ * for libamdhip64's. It keeps the list of launches (kernel, grid, block, LDS) and
  * can make the k-th call of a function fail. No device memory is touched, so
  * any address will do for a buffer. */
 #define _GNU_SOURCE
@@ -12,7 +12,7 @@
 typedef struct { unsigned x, y, z; } dim3_t;
 enum { OK = 0, OUT_OF_MEMORY = 2, MAX_LAUNCHES = 4096 };
 
-static struct { const void* kernel; unsigned long long blocks, threads; } launches[MAX_LAUNCHES];
+static struct { const void* kernel; unsigned long long blocks, threads, shared; } launches[MAX_LAUNCHES];
 static int n_launches, graph_replays;
 static char fail_name[64];
 static int fail_at;
@@ -40,6 +40,7 @@ const char* stub_kernel(int i) {
 }
 unsigned long long stub_blocks(int i) { return launches[i].blocks; }
 unsigned long long stub_threads(int i) { return launches[i].threads; }
+unsigned long long stub_shared(int i) { return launches[i].shared; }
 
 /* launches */
 int __hipPushCallConfiguration(dim3_t g, dim3_t b, size_t sh, void* s) {
@@ -52,11 +53,12 @@ int __hipPopCallConfiguration(dim3_t* g, dim3_t* b, size_t* sh, void** s) {
 }
 static int last;
 int hipLaunchKernel(const void* f, dim3_t g, dim3_t b, void** args, size_t sh, void* s) {
-    (void)args, (void)sh, (void)s;
+    (void)args, (void)s;
     if (n_launches < MAX_LAUNCHES) {
         launches[n_launches].kernel = f;
         launches[n_launches].blocks = (unsigned long long)g.x * g.y * g.z;
         launches[n_launches].threads = (unsigned long long)b.x * b.y * b.z;
+        launches[n_launches].shared = sh;
         n_launches++;
     }
     return last = status(__func__);

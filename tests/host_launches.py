@@ -21,7 +21,8 @@ class Host:
                            check=True)
         self.stub = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
         self.stub.stub_kernel.restype = ctypes.c_char_p
-        self.stub.stub_blocks.restype = self.stub.stub_threads.restype = ctypes.c_ulonglong
+        for f in ("stub_blocks", "stub_threads", "stub_shared"):
+            getattr(self.stub, f).restype = ctypes.c_ulonglong
         sys.modules["torch"] = types.ModuleType("torch")  # the binding imports it for its HIP runtime only
         from paper_2505_17284_amd import _lib
 
@@ -53,6 +54,10 @@ class Host:
     def bind(self, h):
         i = self.info(h)
         return self.lib.sn_plan_bind(h, *self.addresses(i["psi_bytes"], i["psi_bytes"], i["scratch_bytes"]))
+
+    def lds(self):
+        """Dynamic LDS bytes of the launches that launches() is about to return."""
+        return [self.stub.stub_shared(i) for i in range(self.stub.stub_launches())]
 
     def launches(self):
         """[(kernel, blocks, threads per block)] since the last call of this."""

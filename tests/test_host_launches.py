@@ -187,3 +187,21 @@ def test_a_plan_bound_to_the_static_area_and_then_to_caller_scratch(workdir):
     assert static[1] == TWO_STAGES * 2
     assert then[1] == first[1] == ["sn_heun_kernel", "sn_heun_finalize_kernel"] * 2 + ["sn_materialize_kernel",
                                                                                         "sn_pack_kernel"]
+
+
+def _one_pass_launch(host, n, M, order):
+    h = host.plan(I.lattice(n, M, order=order, stepper=I.HEUN))  # noqa: F821
+    host.launches()
+    host.L.check(host.lib.sn_plan_run(h, 1, None), "run")
+    lds = host.lds()[0]
+    return [*host.launches()[0], lds]
+
+
+@pytest.mark.parametrize("n,M", [(1300, 32), (700, 32), (437, 32), (1300, 64), (560, 256)])
+def test_the_last_round_of_one_pass_workgroups_is_not_nearly_empty(workdir, n, M):
+    """Bands are cut for the workgroups that a compute unit holds, by waves (16)
+    and by LDS (160 KiB)."""
+    kernel, blocks, threads, lds = _on_host(workdir, _one_pass_launch, n, M, 3)
+    assert kernel == "sn_heun_kernel"
+    rounds = blocks / (256 * min(1024 // threads, 160 * 1024 // lds))
+    assert rounds % 1 == 0 or rounds % 1 >= 0.4 or rounds > 4, rounds
