@@ -12,8 +12,8 @@ timing starts.
 Prints one JSON line. `value` = cell-ordinate updates per second (one update
 = one (cell, ordinate) advanced one full time step), timed over exactly
 --steps steps with no per-launch instrumentation. `roofline` describes the
-dominant kernel (Heun stage 2; the one-pass Heun step in the Venkatakrishnan
-leg) against 8 TB/s, its average duration taken with HIP events on the launch stream in a second, separately timed pass;
+dominant kernel (Heun stage 2) against 8 TB/s, its average duration taken
+with HIP events on the launch stream in a second, separately timed pass;
 `step_roofline` is the whole step's algorithmic bytes over ms_per_step.
 `cpu_baseline` times the FP64 oracle on a bounded sample of the same
 workload on the host cores. Further keys time the 700^2 x 256 lattice, the
@@ -50,14 +50,14 @@ def source_digest():
 
 
 def measured_traffic(workload, dtype, kernel="stage2"):
-    """HBM bytes per launch of a kernel of the Heun step ("step": the one-pass
-    kernel, "stage2", "stage1") on `workload` from the committed rocprofv3
-    counter summary, or None when the summary is missing or was taken on other
-    sources. The summary is named for the grid and the ordinate count:
-    heun_step_ or stage_heun2_<workload without its stepper suffix>_<dtype>.md."""
+    """HBM bytes per launch of a kernel of the Heun step ("stage2", "stage1") on
+    `workload` from the committed rocprofv3 counter summary, or None when the
+    summary is missing or was taken on other sources. The summary is named for
+    the grid and the ordinate count: stage_heun2_<workload without its stepper
+    suffix>_<dtype>.md."""
     base = workload[: -len("_heun2")] if workload.endswith("_heun2") else workload
     field = "traffic_bytes_per_launch" + ("_stage1" if kernel == "stage1" else "")
-    path = os.path.join(PROFILES, f"{'heun_step' if kernel == 'step' else 'stage_heun2'}_{base}_{dtype}.md")
+    path = os.path.join(PROFILES, f"stage_heun2_{base}_{dtype}.md")
     if not os.path.exists(path):
         return None
     fields = {}

@@ -296,8 +296,9 @@ sn_status sn_batch_run(sn_batch* B, int32_t n_steps, void* stream) {
     // to back, after the shared launches: they fill the GPU by themselves,
     // and consecutive stages of one plan reuse what the cache holds of it. A
     // one-pass step counts its own workgroups (eight lattices of 140^2 and 280^2
-    // with 64 to 256 ordinates: 37 ms all in shared launches, 41 with the
-    // member of 576 stage workgroups on its own, 56 with every member).
+    // with 64 to 256 ordinates, none with as many: 31.9 ms at order 1 and 65.0 at
+    // order 3 all in shared launches; 41.5 and 78.4 with the members of 384 and
+    // more on their own, 50.7 and 96.3 with every member).
     auto step_workgroups = [](const sn_plan* P) { return (int64_t)(P->heun1 ? P->hn_wg : P->n_wg_l[0]); };
     const int64_t direct_min = B->o.direct_min_workgroups < 0
                                    ? INT64_MAX
