@@ -249,6 +249,12 @@ __device__ __forceinline__ float min3f(float a, float b, float c) {
 // a unit in the last place off: other roundings of a factor are amplified by
 // Euler steps until psi parts by 10^-2 of a value (333^2 x 128 lattice, 144 steps;
 // so, 10^-8).
+//
+// SKIP: a wave whose cells all lack a second gradient (empty regions) branches
+// past its two factors. The one-pass kernel does (560^2 x 256 lattice, us a step: 331, 335
+// with a select; 274 while part of the grid is empty), the stage kernels do not
+// (two stages 529 with the branch, 496 with a select; BF16 640 and 583).
+template <bool SKIP>
 __device__ __forceinline__ float venkat_limit(float c, float W, float E, float S, float N, float e2, float& ax,
                                               float& ay) {
     ax = 0.25f * (E - W);
@@ -262,7 +268,13 @@ __device__ __forceinline__ float venkat_limit(float c, float W, float E, float S
     const float t0 = 2.0f * A0, a20 = t0 * A0, t1 = 2.0f * A1, a21 = t1 * A1;
     // A = 0: exactly 1, also where b^2 or e2 is infinite and the quotient a NaN,
     // which fminf passes over
-    const float f0 = A0 == 0.0f ? 1.0f : fminf(venkat_factor(A0, t0, a20, b0, q0), venkat_factor(A0, t0, a20, b1, q1));
+    float f0;
+    if (SKIP) {
+        f0 = A0 == 0.0f ? 1.0f : fminf(venkat_factor(A0, t0, a20, b0, q0), venkat_factor(A0, t0, a20, b1, q1));
+    } else {
+        const float f = fminf(venkat_factor(A0, t0, a20, b0, q0), venkat_factor(A0, t0, a20, b1, q1));
+        f0 = __builtin_unpredictable(A0 == 0.0f) ? 1.0f : f;
+    }
     return fminf(venkat_factor(A1, t1, a21, b0, q0), f0);
 }
 
@@ -491,10 +503,10 @@ __device__ __forceinline__ void loader_edges(SArgs a, int k, char* slot) {
         const char* row = slot + (q + 2) * R::kRowBytes;  // the row's staged cells 0 .. 127
         float e, ax, ay;
         if (sx) {
-            const float L = venkat_limit(hv.y, hv.x, ring_read<T>(row, 0).x, hu.y, hd.y, a.eps2, ax, ay);
+            const float L = venkat_limit<false>(hv.y, hv.x, ring_read<T>(row, 0).x, hu.y, hd.y, a.eps2, ax, ay);
             e = fmaf(L, ax, hv.y);
         } else {
-            const float L = venkat_limit(hv.z, ring_read<T>(row, kWave - 1).y, hv.w, hu.z, hd.z, a.eps2, ax, ay);
+            const float L = venkat_limit<false>(hv.z, ring_read<T>(row, kWave - 1).y, hv.w, hu.z, hd.z, a.eps2, ax, ay);
             e = fmaf(-L, ax, hv.z);
         }
         reinterpret_cast<float*>(slot + R::kEdgeOffset)[q] = e;
@@ -546,7 +558,7 @@ __device__ __forceinline__ void face_flux(const FaceOrd& fo, float eps2, const c
         const float nm = dir ? c0 : c1, np = dir ? c2 : c3;      // its neighbours along the normal
         const float tm = dir ? t1m : t2m, tp = dir ? t1p : t2p;  // and across it
         float gx, gy;
-        const float L = venkat_limit(c, yaxis ? tm : nm, yaxis ? tp : np, yaxis ? nm : tm, yaxis ? np : tp, eps2,
+        const float L = venkat_limit<false>(c, yaxis ? tm : nm, yaxis ? tp : np, yaxis ? nm : tm, yaxis ? np : tp, eps2,
                                      gx, gy);
         tr = first ? c : fmaf(dir ? L : -L, yaxis ? gy : gx, c);
     }
@@ -695,8 +707,8 @@ __device__ __forceinline__ void stage_ordinate(SArgs a, const OrdConst& o, int k
             const float lf = lane_from_left(c1, hv.y);   // cell left of c0
             const float rt = lane_from_right(c0, hv.z);  // cell right of c1
             float ax0, ay0, ax1, ay1;
-            const float L0 = venkat_limit(c0, lf, c1, win[r - 1].x, win[r + 1].x, a.eps2, ax0, ay0);
-            const float L1 = venkat_limit(c1, c0, rt, win[r - 1].y, win[r + 1].y, a.eps2, ax1, ay1);
+            const float L0 = venkat_limit<false>(c0, lf, c1, win[r - 1].x, win[r + 1].x, a.eps2, ax0, ay0);
+            const float L1 = venkat_limit<false>(c1, c0, rt, win[r - 1].y, win[r + 1].y, a.eps2, ax1, ay1);
             {
                 // downwind y-face of row r; on the grid's boundary faces (south
                 // of row 0, north of row ny-1) the upwind cell's own value

@@ -231,7 +231,7 @@ void default_shape(const sn_plan* P, int* group_size, int* group_size_avg, int* 
         // saves): 70^2 x 32 12.0 -> 9.6 us a step, 104^2 x 64 12.4 -> 10.9, 280^2 x
         // 128 32.1 -> 29.5. Orders 2 and 3 would gain as
         // much, but other groups round the scalar flux otherwise, and Euler with
-        // their limiters amplifies that without end (largest difference of psi,
+        // their limiters amplifies that step by step (largest difference of psi,
         // of max(|psi|, rms): 200^2 x 64 lattice 1.2 10^-3 after 144 steps, 208^2 x
         // 64 Hohlraum 1.5 10^-3 after 96 and 7.6 10^-3 after 144).
         int gs = std::min(P->M, 32);
@@ -492,10 +492,10 @@ bool heun_sides(sn_plan* P) {
 // ordinates; 16 waves halve the scalar-flux sums that 8 write, but leave one
 // workgroup per compute unit, which waits at its own barriers: measured (order 1,
 // lattice, us a step with 8 waves and with 16) 2-4% faster from 1.2 10^5 cells on
-// (437^2 x 128 64.8 and 62.9, 700^2 x 256 294 and 287, 1300^2 x 256 949 and 912)
-// and where the ordinates are many (140^2 x 1936 136 and 133), level or slower
-// below (280^2 x 128 41.0 and 41.0, 140^2 x 256 32.6 and 34.2), and 5-9% slower
-// at order 3 (560^2 x 256 274 and 288, 1300^2 x 256 1159 and 1259). The band is the
+// (437^2 x 128 64.9 and 63.0, 700^2 x 256 295 and 288, 1300^2 x 256 950 and 912)
+// and where the ordinates are many (140^2 x 1936 136 and 132), level or slower
+// below (280^2 x 128 41.2 and 40.8, 140^2 x 256 32.7 and 34.2), and 3-9% slower
+// at order 3 (560^2 x 256 327 and 346, 1300^2 x 256 1572 and 1685). The band is the
 // multiple of 4 up to 64 rows (the rows between two barriers) with the least
 //     rounds of workgroups x (rows + 12),
 // 12 rows standing for a march's start (its first loads, three rows before
@@ -634,20 +634,20 @@ sn_status derive(sn_plan* P, int group_size, int group_size_avg, int rows, int w
     // The one-pass Heun step (sn_heun_impl.h) at orders 1 and 3 wherever it
     // can: it is faster at every size measured (lattice, us a step with the
     // finalize against two stages: order 1 70 x 70 x 32 18 to 24, 700 x 700 x 256
-    // 287 to 522; order 3 104 x 104 x 32 27 to 40, 700 x 700 x 256 410 to 699). Not
-    // with BF16 storage (g would be rounded before s is added),
-    // with a reflecting side (a ghost cell is then psi1 of another ordinate) or
-    // probes (their moments are of psi1).
+    // 294 to 521; order 3 104 x 104 x 32 28 to 39, 700 x 700 x 256 532 to 734). Not
+    // with BF16 storage (g would be rounded before s is added), with a reflecting
+    // side (a ghost cell is then psi1 of another ordinate) or probes (their
+    // moments are of psi1).
     // Nor with minmod (order 2), whatever the size, although it would halve a
     // step: the state is rounded in other places, and minmod amplifies any
-    // rounding without end where its two slopes are about equal. Largest
-    // difference to the two stages, of max(|psi|, rms): 4 10^-5, 8 10^-4 and
-    // 5 10^-3 after 24, 48 and 72 steps of the 700^2 x 256 lattice, 1.4 10^-3
-    // after 96 of the 700^2 x 256 cavity, 6 10^-2 after 104 of the 390^2 x 256
-    // Hohlraum. Order 1 contracts (at most 2 10^-6 after 144 steps). Order 3's
-    // limiter is smooth: 2 10^-6 after 96 steps of the 560^2 x 256 lattice; in
-    // void with grazing fronts it amplifies too, but later (390^2 x 128 Hohlraum,
-    // worst of four draws 2 10^-5 after 48 steps, 2 10^-4 after 96, 6 10^-4 after 144).
+    // rounding where its two slopes are about equal, to per cents of a value.
+    // Largest difference to the two stages, of max(|psi|, rms): 4 10^-5, 8 10^-4 and
+    // 5 10^-3 after 24, 48 and 72 steps of the 700^2 x 256 lattice, 2 10^-2 after 288
+    // of the 437^2 x 128 cavity, 6 10^-2 after 104 of the 390^2 x 256 Hohlraum (2-norm
+    // 2 10^-4). Order 1 contracts (at most 2 10^-6 after 144 steps). Order 3's
+    // limiter is smooth: where noise crosses a void it is amplified too, but
+    // decays again (2 10^-5 after 48 steps, 1.2 10^-3 at worst and 2-norm 10^-6 at any of
+    // 48 to 600 steps of a dozen draws), and the forms are level against FP64.
     // Nor where the caller asks for ordinate groups: those are the stage kernels'.
     // (Rows and waves alone do not count: every member of a batch names them.)
     const bool grouped = group_size > 0 || group_size_avg > 0;

@@ -42,8 +42,8 @@ TWO_STAGES = ["sn_stage_kernel", "sn_qoi_finalize_kernel"] * 2
 @pytest.mark.parametrize("kind,n,M", [("lattice", 70, 32), ("lattice", 280, 256), ("lattice", 700, 256),
                                       ("cavity", 437, 128), ("cavity", 1300, 512), ("hohlraum", 390, 256)])
 def test_minmod_heun_steps_are_two_stages_at_every_size(workdir, kind, n, M):
-    """Minmod amplifies a change of rounding without end, so that its steps are
-    the same two launches whatever the size."""
+    """Minmod amplifies a change of rounding to per cents of a value, so that its
+    steps are the same two launches whatever the size."""
     assert _on_host(workdir, _kernels_of_steps, kind, n, M, 2, 1, 3) == TWO_STAGES * 3
 
 
